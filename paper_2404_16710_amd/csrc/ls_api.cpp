@@ -18,8 +18,7 @@ extern "C" int ls_launch_program(const LsKParams* p, int dtype_is_bf16, int grid
 extern "C" int ls_kernel_setup(int dtype_is_bf16, int hd, int* max_blocks_per_cu);
 extern "C" int ls_launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_read(const void* src, size_t bytes, void* sink, int workgroups, hipStream_t stream);
-extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, hipStream_t s);
-extern "C" int ls_prefill_finish(const LsPfParams* p, int last_row, hipStream_t s);
+extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, int last_row, hipStream_t s);
 extern "C" int ls_static_scratch_ptr(void** ptr);
 
 namespace {
@@ -276,7 +275,7 @@ c->kv_policy = 0;
   f.hd = p.hd; f.nkv = p.nkv; f.max_seq = p.max_seq; f.layers_used = p.L; f.eps = p.eps;
   f.embed = w->embed; f.rope_cos = p.rope_cos; f.rope_sin = p.rope_sin; f.kcache = p.kcache; f.vcache = p.vcache;
   f.x_pf = reinterpret_cast<float*>(c->ws + lay.x_pf); f.a_pf = c->ws + lay.a_pf; f.q_pf = c->ws + lay.q_pf;
-  f.o_pf = c->ws + lay.o_pf; f.act_pf = c->ws + lay.act_pf; f.xbuf = p.xbuf; f.ssq = p.ssq;
+  f.o_pf = c->ws + lay.o_pf; f.act_pf = c->ws + lay.act_pf; f.pf_end = c->ws + lay.total; f.n_cu = c->n_cu; f.xbuf = p.xbuf; f.ssq = p.ssq;
   c->gemm_prefill = true;
   return LS_OK;
 }
@@ -339,13 +338,11 @@ static int enqueue_prefill(ls_ctx* c, const int32_t* dev_prompt, int32_t n_promp
   LsPfParams f = c->pf;
   f.ssq_nt = c->base.ssq_nt;
   f.tokens = dev_prompt; f.layers_used = layers_used; f.capture = c->capture;
-  int last_rows = 0;
   for (int pos0 = 0; pos0 < n_prompt; pos0 += c->lay.pf_rows) {
     const int M = n_prompt - pos0 < c->lay.pf_rows ? n_prompt - pos0 : c->lay.pf_rows;
-    if (ls_prefill_layers(&f, c->host_layers.data(), pos0, M, s) != 0) return LS_E_HIP;
-    last_rows = M;
+    const int last_row = pos0 + M == n_prompt ? M - 1 : -1;
+    if (ls_prefill_layers(&f, c->host_layers.data(), pos0, M, last_row, s) != 0) return LS_E_HIP;
   }
-  if (ls_prefill_finish(&f, last_rows - 1, s) != 0) return LS_E_HIP;
   LsKParams p = program(c, LS_PROG_PF_FINISH);
   p.n_tokens = n_prompt; p.out_tokens = dev_out; p.eos = eos; p.max_new = max_new;
   return launch(c, p, s);

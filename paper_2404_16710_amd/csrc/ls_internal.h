@@ -102,10 +102,12 @@ struct LsPfParams {
   const float *rope_cos, *rope_sin;
   void *kcache, *vcache;
   float *x_pf;                 // [pf_rows][dm] residual rows of the chunk
-  void *a_pf, *q_pf, *o_pf, *act_pf;  // [pf_rows][dm], [..][qd], [..][qd], [..][ffn] in the model dtype
+  void *a_pf, *q_pf, *o_pf, *act_pf;  // [pf_rows][dm], [..][qd], [..][qd], [..][ffn] in the model dtype, in this order
+  void *pf_end;                // end of act_pf
+  int32_t n_cu;                // compute units of the device
   float *xbuf, *ssq;           // decode residual row 0 and its statistics (target of the finish step)
   float *capture;
-  int32_t tile_rows;           // rows of a prompt GEMM's output tile: 0 = by the number of tiles, else 32, 64 or 128
+  int32_t tile_rows;           // rows of a prompt GEMM's output tile: 0 = chosen by shape, else 32, 64, 128 or 160
 };
 
 #endif

@@ -12,6 +12,8 @@
 #include <math.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "ls_internal.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -57,30 +59,70 @@ __global__ __launch_bounds__(256) void pf_embed_kernel(const int32_t* tok, const
   for (int k = threadIdx.x; k < dm; k += 256) x[(size_t)m * dm + k] = PT<T>::ld(e + k);
 }
 
-// a[m][k] = T((x[m][k] * rinv_m) * gain[k]),  rinv_m = 1/sqrt(mean_k x[m][k]^2 + eps)
+// Partial sums that a split product left beside the residual rows: x + p[0] + ... + p[n - 1], each [M][dm].
+struct PfParts {
+  const float* p[7];
+  int n;
+};
+
+__device__ __forceinline__ f32x4 pf_row4(const float* x, const PfParts& parts, size_t at) {
+  f32x4 v = *reinterpret_cast<const f32x4*>(x + at);
+  for (int i = 0; i < parts.n; ++i) v += *reinterpret_cast<const f32x4*>(parts.p[i] + at);
+  return v;
+}
+
+// a[m][k] = T((x[m][k] * rinv_m) * gain[k]),  rinv_m = 1/sqrt(mean_k x[m][k]^2 + eps); adds the partial sums of the
+// product before it and writes the complete residual row back.  A row is read once, 16 bytes per lane, and kept in
+// registers between its sum of squares and its scaling up to 8192 columns; bound by memory.
 template <typename T>
-__global__ __launch_bounds__(256) void pf_rmsnorm_kernel(const float* x, const T* gain, T* a, int dm, float eps) {
+__global__ __launch_bounds__(256) void pf_rmsnorm_kernel(float* x, const PfParts parts, const T* gain, T* a, int dm, float eps) {
+  constexpr int NV = 8;
   __shared__ float red[4];
-  const int m = blockIdx.x;
-  const float* xr = x + (size_t)m * dm;
+  const size_t row = (size_t)blockIdx.x * dm;
+  f32x4 v[NV];
   float s = 0.f;
-  for (int k = threadIdx.x; k < dm; k += 256) { const float v = xr[k]; s += v * v; }
+  auto load = [&](int k) {
+    const f32x4 w = pf_row4(x, parts, row + k);
+    if (parts.n) *reinterpret_cast<f32x4*>(x + row + k) = w;
+    s += (w[0] * w[0] + w[1] * w[1]) + (w[2] * w[2] + w[3] * w[3]);
+    return w;
+  };
+  auto store = [&](int k, const f32x4& w, float r) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) PT<T>::st(a + row + k + e, (w[e] * r) * PT<T>::ld(gain + k + e));
+  };
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int k = ((int)threadIdx.x + 256 * i) * 4;
+    v[i] = k < dm ? load(k) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int k = ((int)threadIdx.x + 256 * NV) * 4; k < dm; k += 1024) load(k);
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
   const float tot = (red[0] + red[1]) + (red[2] + red[3]);
   const float r = 1.0f / sqrtf(tot / (float)dm + eps);
-  for (int k = threadIdx.x; k < dm; k += 256) PT<T>::st(a + (size_t)m * dm + k, (xr[k] * r) * PT<T>::ld(gain + k));
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int k = ((int)threadIdx.x + 256 * i) * 4;
+    if (k < dm) store(k, v[i], r);
+  }
+  for (int k = ((int)threadIdx.x + 256 * NV) * 4; k < dm; k += 1024) store(k, *reinterpret_cast<const f32x4*>(x + row + k), r);
 }
 
 // The last prompt row goes to row 0 of the decode residual buffer, with its sum of squares spread
 // over the nt slots the decode kernel's RMSNorm adds up (slot t: columns [t*gs, (t+1)*gs), zero past
 // the end of the row); the head then runs in the decode kernel.
-__global__ __launch_bounds__(256) void pf_finish_kernel(const float* xrow, float* xbuf, float* ssq, int dm, int nt) {
+__global__ __launch_bounds__(256) void pf_finish_kernel(const float* x, const PfParts parts, size_t row, float* xbuf, float* ssq, int dm, int nt) {
   const int gs = (dm + nt - 1) / nt;
   for (int t = threadIdx.x; t < nt; t += 256) {
     float s = 0.f;
-    for (int j = 0; j < gs && t * gs + j < dm; ++j) { const float v = xrow[t * gs + j]; xbuf[t * gs + j] = v; s += v * v; }
+    for (int j = 0; j < gs && t * gs + j < dm; ++j) {
+      float v = x[row + t * gs + j];
+      for (int i = 0; i < parts.n; ++i) v += parts.p[i][row + t * gs + j];
+      xbuf[t * gs + j] = v;
+      s += v * v;
+    }
     ssq[t] = s;
   }
 }
@@ -500,6 +542,7 @@ hipError_t launch_gemm(const PfGemm& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+#include "ls_prompt_mm.inc"
 
 // ------------------------------------------------------------------------------------------
 // Causal attention of the prompt rows on the MFMA units.  One workgroup = 64 query rows of one
@@ -695,28 +738,80 @@ hipError_t launch_attn(const LsPfParams& p, int layer, int pos0, int M, hipStrea
   return hipGetLastError();
 }
 
+// Room for partial sums [M][dm] of a split product in buffers of the prompt pass that are idle during it: whole
+// pieces of `from` .. `end` (contiguous in the workspace).
+static void add_parts(PfMm& g, const void* from, const void* end, size_t piece) {
+  const char* p = static_cast<const char*>(from);
+  for (; g.splits - 1 < kMmParts && p + piece <= static_cast<const char*>(end); p += piece, ++g.splits)
+    g.part[g.splits - 1] = reinterpret_cast<float*>(const_cast<char*>(p));
+}
+
 template <typename T>
-int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, hipStream_t s) {
+int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts& parts, hipStream_t s) {
   const int dm = p.dm, qd = p.qd, kvd = p.kvd, ffn = p.ffn;
+  const bool auto_tiles = p.tile_rows == 0;
   pf_embed_kernel<T><<<dim3(M), dim3(256), 0, s>>>(p.tokens + pos0, static_cast<const T*>(p.embed), p.x_pf, dm, p.vocab);
+  parts.n = 0;
+  // x += A W^T, in as many splits of K as there is room for partial sums in [from, end) and in [from2, end2); what
+  // the splits left is added by the next reader of the rows.  A capture wants complete rows: no splits.
+  auto residual = [&](const void* A, int K, const void* W, float* capture, const void* from, const void* end,
+                      const void* from2, const void* end2) {
+    if (auto_tiles && mm_fits(K, sizeof(T))) {
+      if constexpr (sizeof(T) == 2) {
+        PfMm g{};
+        g.A = A; g.lda = K; g.W[0] = W; g.M = M; g.N = dm; g.K = K; g.x = p.x_pf; g.capture = capture; g.pos0 = pos0; g.hd = p.hd;
+        g.splits = 1;
+        if (p.capture == nullptr) {
+          const size_t piece = (size_t)M * dm * sizeof(float);
+          add_parts(g, from, end, piece);
+          add_parts(g, from2, end2, piece);
+        }
+        if (mm_launch<T, EPI_RESID>(g, p.n_cu, s) != hipSuccess) return false;
+        parts.n = g.splits - 1;
+        for (int i = 0; i < parts.n; ++i) parts.p[i] = g.part[i];
+        return true;
+      }
+    }
+    PfGemm g{};
+    g.A = A; g.lda = K; g.W = W; g.M = M; g.N = dm; g.K = K; g.x = p.x_pf; g.capture = capture; g.pos0 = pos0; g.hd = p.hd;
+    g.tile_rows = p.tile_rows;
+    return launch_gemm<T, EPI_RESID>(g, s) == hipSuccess;
+  };
+  auto norm = [&](const void* gain) {
+    pf_rmsnorm_kernel<T><<<dim3(M), dim3(256), 0, s>>>(p.x_pf, parts, static_cast<const T*>(gain), static_cast<T*>(p.a_pf), dm, p.eps);
+    parts.n = 0;
+  };
   for (int l = 0; l < p.layers_used; ++l) {
     const LsLayerW& W = lw[l];
-    pf_rmsnorm_kernel<T><<<dim3(M), dim3(256), 0, s>>>(p.x_pf, static_cast<const T*>(W.attn_norm), static_cast<T*>(p.a_pf), dm, p.eps);
+    norm(W.attn_norm);
     PfGemm g{};
     g.A = p.a_pf; g.lda = dm; g.M = M; g.K = dm; g.hd = p.hd; g.pos0 = pos0; g.max_seq = p.max_seq; g.nkv = p.nkv;
     g.layer = l; g.rope_cos = p.rope_cos; g.rope_sin = p.rope_sin; g.tile_rows = p.tile_rows;
     g.W = W.wq; g.N = qd; g.out = p.q_pf; g.ldo = qd;
-    bool fused = false;
-    if (qd % BN == 0 && kvd % BN == 0) {
+    bool done = false;
+    PfMm f{};
+    const bool mm = auto_tiles && mm_fits(dm, sizeof(T));
+    if (mm) {
+      const size_t lofs = (size_t)l * p.nkv * p.max_seq * p.hd;
+      f.A = p.a_pf; f.lda = dm; f.M = M; f.K = dm; f.splits = 1; f.hd = p.hd; f.pos0 = pos0; f.max_seq = p.max_seq;
+      f.rope_cos = p.rope_cos; f.rope_sin = p.rope_sin;
+      f.W[0] = W.wq; f.W[1] = W.wk; f.W[2] = W.wv; f.N = qd + 2 * kvd; f.N_q = qd; f.N_kv = kvd;
+      f.out = p.q_pf; f.ldo = qd; f.out_k = static_cast<T*>(p.kcache) + lofs; f.out_v = static_cast<T*>(p.vcache) + lofs;
+      if constexpr (sizeof(T) == 2) {
+        if (mm_launch<T, EPI_QKV>(f, p.n_cu, s) != hipSuccess) return 1;
+      }
+      done = true;
+    }
+    if (!done && qd % BN == 0 && kvd % BN == 0) {
       // one launch for the three projections, when it would run on the large tiles anyway
-      PfGemm f = g;
-      f.W2 = W.wk; f.W3 = W.wv; f.N = qd + 2 * kvd; f.N_q = qd; f.N_kv = kvd; f.out_k = p.kcache; f.out_v = p.vcache;
-      if (!use_small_tiles(f) && !use_small_tiles(g)) {
-        if (launch_gemm<T, EPI_QKV>(f, s) != hipSuccess) return 1;
-        fused = true;
+      PfGemm h = g;
+      h.W2 = W.wk; h.W3 = W.wv; h.N = qd + 2 * kvd; h.N_q = qd; h.N_kv = kvd; h.out_k = p.kcache; h.out_v = p.vcache;
+      if (!use_small_tiles(h) && !use_small_tiles(g)) {
+        if (launch_gemm<T, EPI_QKV>(h, s) != hipSuccess) return 1;
+        done = true;
       }
     }
-    if (!fused) {
+    if (!done) {
       if (launch_gemm<T, EPI_ROPE_Q>(g, s) != hipSuccess) return 1;
       g.W = W.wk; g.N = kvd; g.out = p.kcache;
       if (launch_gemm<T, EPI_ROPE_K>(g, s) != hipSuccess) return 1;
@@ -724,26 +819,34 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, hipStre
       if (launch_gemm<T, EPI_V>(g, s) != hipSuccess) return 1;
     }
     if (launch_attn<T>(p, l, pos0, M, s) != hipSuccess) return 1;
-    g.A = p.o_pf; g.lda = qd; g.K = qd; g.W = W.wo; g.N = dm; g.x = p.x_pf; g.capture = nullptr;
-    if (launch_gemm<T, EPI_RESID>(g, s) != hipSuccess) return 1;
-    pf_rmsnorm_kernel<T><<<dim3(M), dim3(256), 0, s>>>(p.x_pf, static_cast<const T*>(W.ffn_norm), static_cast<T*>(p.a_pf), dm, p.eps);
-    g.A = p.a_pf; g.lda = dm; g.K = dm; g.W = W.wg; g.W2 = W.wu; g.N = ffn; g.out = p.act_pf; g.ldo = ffn;
-    if (launch_gemm<T, EPI_GU>(g, s) != hipSuccess) return 1;
-    g.A = p.act_pf; g.lda = ffn; g.K = ffn; g.W = W.wd; g.W2 = nullptr; g.N = dm; g.x = p.x_pf;
-    g.capture = p.capture ? p.capture + (size_t)l * p.max_seq * dm : nullptr;
-    if (launch_gemm<T, EPI_RESID>(g, s) != hipSuccess) return 1;
+    // (workspace order: x, a, q, o, act.  q and act are idle from here to the end of the next norm, q and o from the
+    // down projection to the end of its norm; a is what the norm writes.)
+    if (!residual(p.o_pf, qd, W.wo, nullptr, p.act_pf, p.pf_end, p.q_pf, p.o_pf)) return 1;
+    norm(W.ffn_norm);
+    if (mm) {
+      f.W[0] = W.wg; f.W[1] = W.wu; f.N = ffn; f.out = p.act_pf; f.ldo = ffn; f.splits = 1;
+      if constexpr (sizeof(T) == 2) {
+        if (mm_launch<T, EPI_GU>(f, p.n_cu, s) != hipSuccess) return 1;
+      }
+    } else {
+      g.A = p.a_pf; g.lda = dm; g.K = dm; g.W = W.wg; g.W2 = W.wu; g.N = ffn; g.out = p.act_pf; g.ldo = ffn;
+      if (launch_gemm<T, EPI_GU>(g, s) != hipSuccess) return 1;
+    }
+    float* capture = p.capture ? p.capture + (size_t)l * p.max_seq * dm : nullptr;
+    if (!residual(p.act_pf, ffn, W.wd, capture, p.q_pf, p.act_pf, nullptr, nullptr)) return 1;
   }
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
 }  // namespace
 
-// Runs layers 0..layers_used-1 over rows [pos0, pos0+M) of the prompt (M <= pf_rows).
-extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, hipStream_t s) {
-  return p->is_bf16 ? run_layers<bf16_t>(*p, host_layers, pos0, M, s) : run_layers<float>(*p, host_layers, pos0, M, s);
-}
-
-extern "C" int ls_prefill_finish(const LsPfParams* p, int last_row, hipStream_t s) {
-  pf_finish_kernel<<<dim3(1), dim3(256), 0, s>>>(p->x_pf + (size_t)last_row * p->dm, p->xbuf, p->ssq, p->dm, p->ssq_nt);
+// Runs layers 0..layers_used-1 over rows [pos0, pos0+M) of the prompt (M <= pf_rows) and, after the last chunk,
+// hands row `last_row` of it to the decode kernel (last_row < 0: more chunks follow).
+extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, int last_row, hipStream_t s) {
+  PfParts parts{};
+  const int rc = p->is_bf16 ? run_layers<bf16_t>(*p, host_layers, pos0, M, parts, s)
+                            : run_layers<float>(*p, host_layers, pos0, M, parts, s);
+  if (rc != 0 || last_row < 0) return rc;
+  pf_finish_kernel<<<dim3(1), dim3(256), 0, s>>>(p->x_pf, parts, (size_t)last_row * p->dm, p->xbuf, p->ssq, p->dm, p->ssq_nt);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
