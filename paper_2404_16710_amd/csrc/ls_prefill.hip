@@ -547,6 +547,8 @@ hipError_t launch_gemm(const PfGemm& g, hipStream_t s) {
 #include "ls_prompt_mm.inc"
 
 // ------------------------------------------------------------------------------------------
+#include "ls_prompt_attn.inc"
+
 // Causal attention of the prompt rows on the MFMA units.  One workgroup = 64 query rows of one
 // query head (a wave = 16 of them); K/V tiles of TK positions are staged in LDS (V transposed, so
 // that both operands of both products are contiguous along the contracted index) and folded in
@@ -556,36 +558,8 @@ hipError_t launch_gemm(const PfGemm& g, hipStream_t s) {
 // so a lane keeps one query's statistics: lane (c = lane & 15, g = lane >> 4) holds S^T rows
 // 4g..4g+3 of column c for each 16-key block, which are exactly the slots 8g..8g+7 of the P^T
 // operand when a 32-key half is numbered (block 0: keys 4g..4g+3, block 1: keys 16+4g..16+4g+3);
-// the V^T operand is read from LDS in that order.  Probabilities stay fp32 in effect: for bf16
-// models P is fed as a bf16 head plus a bf16 remainder (two products), scores, statistics and the
-// output accumulate in fp32; the output is rounded to the model dtype on store, like the decode path.
+// the V^T operand is read from LDS in that order.  For fp32 models; 16-bit ones take pf_attn16_kernel.
 template <typename T> struct AT;
-template <> struct AT<bf16_t> {
-  struct Op { uint4 v; };
-  static __device__ __forceinline__ Op ld8(const bf16_t* p) { Op o; o.v = *reinterpret_cast<const uint4*>(p); return o; }
-  static __device__ __forceinline__ Op ld44(const bf16_t* p0, const bf16_t* p1) {
-    const uint2 a = *reinterpret_cast<const uint2*>(p0), b = *reinterpret_cast<const uint2*>(p1);
-    Op o; o.v = make_uint4(a.x, a.y, b.x, b.y); return o;
-  }
-  static __device__ __forceinline__ void mma(f32x4& acc, const Op& a, const Op& b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.v), __builtin_bit_cast(bf16x8, b.v), acc, 0, 0, 0);
-  }
-  static __device__ __forceinline__ void mma_p(f32x4& acc, const Op& a, const float* p) {
-    uint32_t hi[8], lo[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { hi[j] = f2bf(p[j]); lo[j] = f2bf(p[j] - bf2f(hi[j])); }
-    Op h, l;
-    h.v = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-    l.v = make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
-    mma(acc, a, h);
-    mma(acc, a, l);
-  }
-  static __device__ __forceinline__ void scatter(bf16_t* vt, int stride, const uint4& v) {  // 8 elements, one per row
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) vt[e * stride] = (bf16_t)((w[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu);
-  }
-};
 template <> struct AT<float> {
   struct Op { float f[8]; };
   static __device__ __forceinline__ Op ld8(const float* p) {
@@ -615,7 +589,7 @@ __global__ __launch_bounds__(256) void pf_attn_kernel(const T* __restrict__ q, T
                                                       const T* __restrict__ kc, const T* __restrict__ vc, int M,
                                                       int pos0, int qd, int G, int max_seq, float scale) {
   constexpr int EPV = 16 / (int)sizeof(T);          // elements per 16 bytes
-  constexpr int TK = sizeof(T) == 2 ? 64 : 32;      // positions per K/V tile
+  constexpr int TK = 32;                            // positions per K/V tile
   constexpr int KB16 = TK / 16, HF = TK / 32, KS = HD / 32, DB = HD / 16;
   constexpr int KROW = HD + EPV;                    // padded rows: conflict-free 16-byte reads down a column of rows
   constexpr int VROW = TK + 4;
@@ -731,13 +705,15 @@ hipError_t launch_attn(const LsPfParams& p, int layer, int pos0, int M, hipStrea
   const size_t lofs = (size_t)layer * p.nkv * p.max_seq * p.hd;
   const T* kc = static_cast<const T*>(p.kcache) + lofs;
   const T* vc = static_cast<const T*>(p.vcache) + lofs;
-  const float scale = (float)(1.0 / sqrt((double)p.hd));
-  dim3 grid((M + 63) / 64, nq);
-  if (p.hd == 128)
-    pf_attn_kernel<T, 128><<<grid, dim3(256), 0, s>>>(static_cast<const T*>(p.q_pf), static_cast<T*>(p.o_pf), kc, vc, M, pos0, p.qd, G, p.max_seq, scale);
-  else
-    pf_attn_kernel<T, 64><<<grid, dim3(256), 0, s>>>(static_cast<const T*>(p.q_pf), static_cast<T*>(p.o_pf), kc, vc, M, pos0, p.qd, G, p.max_seq, scale);
-  return hipGetLastError();
+  if constexpr (sizeof(T) == 2) {
+    return p.hd == 128 ? attn16<128>(p, kc, vc, pos0, M, s) : attn16<64>(p, kc, vc, pos0, M, s);
+  } else {
+    const float scale = (float)(1.0 / sqrt((double)p.hd));
+    const dim3 grid((M + 63) / 64, nq);
+    const auto kernel = p.hd == 128 ? pf_attn_kernel<T, 128> : pf_attn_kernel<T, 64>;
+    kernel<<<grid, dim3(256), 0, s>>>(static_cast<const T*>(p.q_pf), static_cast<T*>(p.o_pf), kc, vc, M, pos0, p.qd, G, p.max_seq, scale);
+    return hipGetLastError();
+  }
 }
 
 // Room for partial sums [M][dm] of a split product in buffers of the prompt pass that are idle during it: whole
