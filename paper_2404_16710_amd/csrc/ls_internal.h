@@ -15,6 +15,9 @@
 #define LS_RED_BYTES 8192        // LDS bytes for the cross-wave reduction of accumulator tiles
 #define LS_SMEM_BYTES (LS_ACT_BYTES + LS_RED_BYTES + LS_MISC_BYTES)
 
+#define LS_BAR_COUNTERS 576      // words of LsKParams::bar that the grid barrier may use
+#define LS_ATTN_COUNTERS (1024 - LS_BAR_COUNTERS) // (block of queries, KV head) pairs that can be counted behind them
+
 // Size of the library's own workspace array (ls_generate_static): enough for tiny models only.
 #define LS_STATIC_SCRATCH_BYTES (8u << 20)
 
@@ -70,7 +73,8 @@ struct LsKParams {
   int32_t kv_through_caches;        // settled K/V tiles are read with cacheable loads: set when the whole KV cache
                                     // is small enough to stay in the memory-side cache between passes
   float *cand;                      // [grid][16][4]
-  uint32_t *bar;                    // grid barrier counters (4096 bytes)
+  uint32_t *bar;                    // grid barrier counters (LS_BAR_COUNTERS words), then LS_ATTN_COUNTERS attention counters;
+                                    // 4096 bytes, zero at launch
   LsState *state;
   float *capture;                   // [L][max_seq][dm] or null
   // ssq_nt: sums of squares per residual row (the number of workgroups); x_tiles: most weight tiles
