@@ -89,6 +89,16 @@ struct PfParts {
   int n;
 };
 
+// The complete residual rows of a captured layer.
+__global__ __launch_bounds__(256) void pf_capture_kernel(const float* x, const PfParts parts, float* capture, int dm) {
+  const size_t row = (size_t)blockIdx.x * dm;
+  for (int k = 4 * (int)threadIdx.x; k < dm; k += 1024) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(x + row + k);
+    for (int i = 0; i < parts.n; ++i) v += *reinterpret_cast<const f32x4*>(parts.p[i] + row + k);
+    *reinterpret_cast<f32x4*>(capture + row + k) = v;
+  }
+}
+
 // a[m][k] = T((x[m][k] * rinv_m) * gain[k]),  rinv_m = 1/sqrt(mean_k x[m][k]^2 + eps); adds the partial sums of the
 // product before it and writes the complete residual row back.  A row is read once, 16 bytes per lane, and kept in
 // registers between its sum of squares and its scaling up to 1024 NV columns (longer rows: read again).  Bound by
@@ -808,22 +818,23 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts
   pf_embed_kernel<T><<<dim3(M), dim3(256), 0, s>>>(p.tokens + pos0, static_cast<const T*>(p.embed), p.x_pf, dm, p.vocab);
   parts.n = 0;
   // x += A W^T, in as many splits of K as there is room for partial sums in [from, end) and in [from2, end2); what
-  // the splits left is added by the next reader of the rows.  A capture wants complete rows: no splits.
+  // the splits left is added by the next reader of the rows.  A capture changes nothing but that the complete rows are
+  // also written there, so a captured pass leaves the same bits as one that is not.
   auto residual = [&](const void* A, int K, const void* W, float* capture, const void* from, const void* end,
                       const void* from2, const void* end2) {
     if (auto_tiles && mm_fits(K, sizeof(T))) {
       if constexpr (sizeof(T) == 2) {
         PfMm g{};
-        g.A = A; g.lda = K; g.W[0] = W; g.M = M; g.N = dm; g.K = K; g.x = p.x_pf; g.capture = capture; g.pos0 = pos0; g.hd = p.hd;
+        g.A = A; g.lda = K; g.W[0] = W; g.M = M; g.N = dm; g.K = K; g.x = p.x_pf; g.pos0 = pos0; g.hd = p.hd;
         g.splits = 1;
-        if (p.capture == nullptr) {
-          const size_t piece = (size_t)M * dm * sizeof(float);
-          add_parts(g, from, end, piece);
-          add_parts(g, from2, end2, piece);
-        }
+        const size_t piece = (size_t)M * dm * sizeof(float);
+        add_parts(g, from, end, piece);
+        add_parts(g, from2, end2, piece);
         if (mm_launch<T, EPI_RESID>(g, p.n_cu, s) != hipSuccess) return false;
         parts.n = g.splits - 1;
         for (int i = 0; i < parts.n; ++i) parts.p[i] = g.part[i];
+        if (capture != nullptr)
+          pf_capture_kernel<<<dim3(M), dim3(256), 0, s>>>(p.x_pf, parts, capture + (size_t)pos0 * dm, dm);
         return true;
       }
     }

@@ -1,6 +1,6 @@
 """The prompt pass's matrix products with tiles sent straight into LDS, at the sizes where they can go
 wrong: one row past and one short of a tile height, ragged last tiles in rows and columns, heads of
-both widths, products whose K is split over several workgroups (no capture) and not (capture), and
+both widths, products whose K is split over several workgroups, with a capture and without, and
 row counts that reach the tallest tile.  Reference: the CPU oracle."""
 import numpy as np
 import pytest
@@ -42,7 +42,7 @@ def test_prompt_products_match_oracle(w):
     gm.debug_capture(False)
     for l in range(L):
         assert rel_err_rows(got[l], ref.hidden[l + 1][:w.n_prompt]) < 2e-2, l
-    gm.prefill(prompt)                                   # no capture: K may be split
+    gm.prefill(prompt)
     _, last, _ = gm.get_state()
     if ref.margins[0] >= NEAR_TIE:
         assert last == ref.tokens[0]
@@ -78,3 +78,23 @@ def test_scores_of_all_rows_at_once_match_the_row_passes(n, kw):
     probe, pm = gm.probe_layers(seq)
     assert list(probe[L - 1]) == list(got) and list(pm[L - 1]) == list(m)     # bit for bit
     gm.close()
+
+
+# One prompt pass with a capture of the hidden states and one without leave the same cache, bit for bit, also where the
+# products' K is split (so that a captured job has the ids of the same job without it).
+@pytest.mark.parametrize("n", [33, 129, 300])
+def test_a_captured_prompt_pass_is_the_same_pass(n):
+    from paper_2404_16710_amd import LsModel
+    w = _case("capture", n, d_model=512, ffn_dim=4096)
+    ws, prompt = W.make_weights(w), W.make_prompt(w)
+    gm = LsModel(w.model, ws, max_seq=n + 17)
+    margins = []
+    for on in (False, True, False):
+        gm.debug_capture(on)
+        gm.prefill(prompt)
+        gm.draft(w.model.n_layers, 6)
+        ids, _, m, _, _ = gm.peek_round(6)
+        margins.append((list(ids), [float(x) for x in m]))
+    gm.debug_capture(False)
+    gm.close()
+    assert margins[0] == margins[1] == margins[2]
