@@ -19,8 +19,6 @@ extern "C" int ls_kernel_setup(int dtype_is_bf16, int hd, int* max_blocks_per_cu
 extern "C" int ls_launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_read(const void* src, size_t bytes, void* sink, int workgroups, hipStream_t stream);
 extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, int last_row, hipStream_t s);
-extern "C" int ls_prefill_scores(const LsPfParams* p, int n);
-extern "C" int ls_prefill_clear_state(LsState* st, hipStream_t s);
 extern "C" int ls_static_scratch_ptr(void** ptr);
 
 namespace {
@@ -277,8 +275,7 @@ c->kv_policy = 0;
   f.hd = p.hd; f.nkv = p.nkv; f.max_seq = p.max_seq; f.layers_used = p.L; f.eps = p.eps;
   f.embed = w->embed; f.rope_cos = p.rope_cos; f.rope_sin = p.rope_sin; f.kcache = p.kcache; f.vcache = p.vcache;
   f.x_pf = reinterpret_cast<float*>(c->ws + lay.x_pf); f.a_pf = c->ws + lay.a_pf; f.q_pf = c->ws + lay.q_pf;
-  f.o_pf = c->ws + lay.o_pf; f.act_pf = c->ws + lay.act_pf; f.pf_end = c->ws + lay.total; f.n_cu = c->n_cu;
-  f.final_norm = w->final_norm; f.lm_head = w->lm_head; f.xbuf = p.xbuf; f.ssq = p.ssq;
+  f.o_pf = c->ws + lay.o_pf; f.act_pf = c->ws + lay.act_pf; f.pf_end = c->ws + lay.total; f.n_cu = c->n_cu; f.xbuf = p.xbuf; f.ssq = p.ssq;
   c->gemm_prefill = true;
   return LS_OK;
 }
@@ -471,26 +468,11 @@ static int score_impl(ls_ctx* c, const int32_t* dev_tokens, int32_t n, int32_t l
   if (n < 1 || layers_used < 1 || layers_used > c->cfg.n_layers) return LS_E_RANGE;
   if (n > c->cfg.max_seq) return LS_E_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int rc;
-  // As many rows as the prompt pass takes run through it, with the head product on all rows of a chunk at once (1.5B
-  // shape, 777 tokens: 98.7 ms in 16-row passes, each of which reads every weight; a timeline is one of those passes).
-  if (c->gemm_prefill && n >= kPrefillMinRows && c->prof == nullptr && ls_prefill_scores(&c->pf, n)) {
-    LsPfParams f = c->pf;
-    f.ssq_nt = c->base.ssq_nt;
-    f.tokens = dev_tokens; f.n_tokens = n; f.layers_used = layers_used; f.capture = c->capture;
-    f.score = probe ? LS_PF_PROBE : LS_PF_SCORE; f.out_tokens = dev_argmax; f.out_margin = dev_margin;
-    for (int pos0 = 0; pos0 < n; pos0 += c->lay.pf_rows) {
-      const int M = n - pos0 < c->lay.pf_rows ? n - pos0 : c->lay.pf_rows;
-      if (ls_prefill_layers(&f, c->host_layers.data(), pos0, M, -1, s) != 0) return LS_E_HIP;
-    }
-    if (ls_prefill_clear_state(c->base.state, s) != 0) return LS_E_HIP;
-  } else {
-    LsKParams p = program(c, LS_PROG_SCORE);
-    p.probe = probe ? 1 : 0;
-    p.tokens = dev_tokens; p.n_tokens = n; p.layers_used = layers_used; p.out_tokens = dev_argmax; p.out_margin = dev_margin;
-    rc = launch(c, p, s);
-    if (rc != LS_OK) return rc;
-  }
+  LsKParams p = program(c, LS_PROG_SCORE);
+  p.probe = probe ? 1 : 0;
+  p.tokens = dev_tokens; p.n_tokens = n; p.layers_used = layers_used; p.out_tokens = dev_argmax; p.out_margin = dev_margin;
+  int rc = launch(c, p, s);
+  if (rc != LS_OK) return rc;
   c->prefilled = false; c->drafted = false;
   LsState st;
   rc = read_state(c, &st, s);

@@ -96,8 +96,6 @@ struct LsKParams {
   int32_t prof_cap, prof_wg;
 };
 
-enum { LS_PF_PROMPT = 0, LS_PF_SCORE = 1, LS_PF_PROBE = 2 };
-
 // Parameters of the GEMM prefill (host side launches; see ls_prefill.hip).
 struct LsPfParams {
   int32_t is_bf16, dm, qd, kvd, ffn, vocab, hd, nkv, max_seq, layers_used;
@@ -113,12 +111,6 @@ struct LsPfParams {
   int32_t n_cu;                // compute units of the device
   float *xbuf, *ssq;           // decode residual row 0 and its statistics (target of the finish step)
   float *capture;
-  // scoring: the head on every row, after the last layer (LS_PF_SCORE) or after every one (LS_PF_PROBE, outputs
-  // [layer][n_tokens])
-  int32_t score, n_tokens;
-  const void *final_norm, *lm_head;
-  int32_t *out_tokens;
-  float *out_margin;
   int32_t tile_rows;           // rows of a prompt GEMM's output tile: 0 = chosen by shape, else 32, 64, 128 or 160
 };
 

@@ -9,9 +9,7 @@
 // all accumulation are fp32.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <limits.h>
 #include <math.h>
-#include <stddef.h>
 #include <stdlib.h>
 
 #include <type_traits>
@@ -193,7 +191,7 @@ __global__ __launch_bounds__(256) void pf_finish_kernel(const float* x, const Pf
 // of the tile width there, so a tile never straddles two matrices).  Three launches of 640 tiles each
 // (13B shape, 1024 prompt rows) fill the 512 resident workgroups one and a quarter times each; one
 // launch of 1920 tiles fills them three and three quarter times.
-enum { EPI_ROPE_Q = 0, EPI_ROPE_K = 1, EPI_V = 2, EPI_RESID = 3, EPI_GU = 4, EPI_QKV = 5, EPI_HEAD = 6 };
+enum { EPI_ROPE_Q = 0, EPI_ROPE_K = 1, EPI_V = 2, EPI_RESID = 3, EPI_GU = 4, EPI_QKV = 5 };
 
 struct PfGemm {
   const void* A;    // [M][K] activations (model dtype), row stride lda
@@ -782,35 +780,6 @@ static void add_parts(PfMm& g, const void* from, const void* end, size_t piece) 
     g.part[g.splits - 1] = reinterpret_cast<float*>(const_cast<char*>(p));
 }
 
-// Rows of one head product: what the candidates of every row leave room for behind the rows that it reads.
-static int head_rows(const LsPfParams& p, int M) {
-  const size_t room = (size_t)(static_cast<const char*>(p.pf_end) - static_cast<const char*>(p.q_pf));
-  int rows = M;
-  while (rows > 0 && (size_t)rows * mm_head_cols(rows, p.vocab, p.dm, p.n_cu) * sizeof(PfCand) > room) rows /= 2;
-  return rows;
-}
-
-// g(x) of every row of the chunk: final norm, head product, token and margin per row.  `out`: index of the first row.
-template <typename T>
-int run_head(const LsPfParams& p, int M, PfParts& parts, size_t out, hipStream_t s) {
-  launch_rmsnorm<T>(p.x_pf, parts, p.final_norm, p.a_pf, M, p.dm, p.eps, s);
-  parts.n = 0;
-  if constexpr (sizeof(T) == 2) {
-    const int step = head_rows(p, M);
-    for (int m = 0; m < M; m += step) {
-      PfMm g{};
-      g.A = static_cast<const T*>(p.a_pf) + (size_t)m * p.dm; g.lda = p.dm; g.W[0] = p.lm_head;
-      g.M = M - m < step ? M - m : step; g.N = p.vocab; g.K = p.dm; g.splits = 1; g.hd = p.hd;
-      g.cand = static_cast<PfCand*>(p.q_pf);
-      const int cols = mm_head_cols(g.M, p.vocab, p.dm, p.n_cu);
-      if (mm_launch<T, EPI_HEAD>(g, p.n_cu, s) != hipSuccess) return 1;
-      pf_pick_kernel<<<dim3((g.M + 3) / 4), dim3(256), 0, s>>>(g.cand, cols, g.M, p.out_tokens + out + m,
-                                                              p.out_margin ? p.out_margin + out + m : nullptr);
-    }
-  }
-  return 0;
-}
-
 template <typename T>
 int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts& parts, hipStream_t s) {
   const int dm = p.dm, qd = p.qd, kvd = p.kvd, ffn = p.ffn;
@@ -900,8 +869,6 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts
     }
     float* capture = p.capture ? p.capture + (size_t)l * p.max_seq * dm : nullptr;
     if (!residual(p.act_pf, ffn, W.wd, capture, p.q_pf, p.act_pf, nullptr, nullptr)) return 1;
-    const bool head = p.score == LS_PF_PROBE || (p.score == LS_PF_SCORE && l + 1 == p.layers_used);
-    if (head && run_head<T>(p, M, parts, p.score == LS_PF_PROBE ? (size_t)l * p.n_tokens + pos0 : (size_t)pos0, s) != 0) return 1;
   }
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
@@ -916,25 +883,5 @@ extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layer
                             : run_layers<float>(*p, host_layers, pos0, M, parts, s);
   if (rc != 0 || last_row < 0) return rc;
   pf_finish_kernel<<<dim3((p->ssq_nt + 3) / 4), dim3(256), 0, s>>>(p->x_pf, parts, (size_t)last_row * p->dm, p->xbuf, p->ssq, p->dm, p->ssq_nt);
-  return hipGetLastError() == hipSuccess ? 0 : 1;
-}
-
-// Can the head of every row (scoring, the layer probe) run here?  16-bit rows of whole steps, and room for the
-// candidates of a useful number of rows.
-extern "C" int ls_prefill_scores(const LsPfParams* p, int n) {
-  if (!p->is_bf16 || p->tile_rows != 0 || !mm_fits(p->dm, 2)) return 0;
-  const int rows = n < 64 ? n : 64;
-  return head_rows(*p, rows) == rows;
-}
-
-// What the last pass of the decode kernel leaves after scoring: no decoding state, the error flag as it was.
-__global__ void pf_clear_state_kernel(LsState* st) {
-  const int n = (int)(sizeof(LsState) / 4), keep = (int)(offsetof(LsState, error) / 4);
-  for (int i = threadIdx.x; i < n; i += 64)
-    if (i != keep) reinterpret_cast<int32_t*>(st)[i] = 0;
-}
-
-extern "C" int ls_prefill_clear_state(LsState* st, hipStream_t s) {
-  pf_clear_state_kernel<<<dim3(1), dim3(64), 0, s>>>(st);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }

@@ -56,30 +56,6 @@ def test_prompt_products_match_oracle(w):
     gm.close()
 
 
-# vocabularies with a ragged last tile; one so large that the candidates of all rows do not fit the idle buffers and
-# the head runs in groups of rows; a text of two chunks (2048 + 60 rows)
-@pytest.mark.parametrize("n, kw", [(32, {}), (65, {}), (300, {}), (300, dict(vocab=32016)),
-                                   (2108, dict(d_model=128, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=320))])
-def test_scores_of_all_rows_at_once_match_the_row_passes(n, kw):
-    from paper_2404_16710_amd import LsModel
-    w = _case("score", n, **kw)
-    ws, seq = W.make_weights(w), W.make_prompt(w)
-    gm = LsModel(w.model, ws, max_seq=n + 1)
-    L = w.model.n_layers
-    gm.set_prompt_tiles(16)
-    want, wm = gm.score(seq)
-    gm.set_prompt_tiles(0)
-    got, m = gm.score(seq)
-    want, wm, got, m = map(np.asarray, (want, wm, got, m))
-    # a logit moves by rounding noise of 16-bit activations (below half the band; see parity_util)
-    assert np.abs(m - wm).max() < NOISE_BAND
-    assert not ((got != want) & (wm >= NOISE_BAND)).any()
-    assert (got == want).mean() > 0.9
-    probe, pm = gm.probe_layers(seq)
-    assert list(probe[L - 1]) == list(got) and list(pm[L - 1]) == list(m)     # bit for bit
-    gm.close()
-
-
 # One prompt pass with a capture of the hidden states and one without leave the same cache, bit for bit, also where the
 # products' K is split (so that a captured job has the ids of the same job without it).
 @pytest.mark.parametrize("n", [33, 129, 300])
