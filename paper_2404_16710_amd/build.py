@@ -27,7 +27,7 @@ FLAGS = [
     # scratch traffic per workgroup each way, about 10 us per pass); a call that carries the "tail"
     # marker is excluded from that, hence no sibling-call marking.
     "-mllvm", "-enable-ipra", "-fno-optimize-sibling-calls",
-    "-Wno-unused-command-line-argument", "-Wno-inline-asm", "-Wno-unknown-warning-option",
+    "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
 ]
 
 
