@@ -468,10 +468,12 @@ static int score_impl(ls_ctx* c, const int32_t* dev_tokens, int32_t n, int32_t l
   if (n < 1 || layers_used < 1 || layers_used > c->cfg.n_layers) return LS_E_RANGE;
   if (n > c->cfg.max_seq) return LS_E_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  int rc = recover(c, s);
+  if (rc != LS_OK) return rc;
   LsKParams p = program(c, LS_PROG_SCORE);
   p.probe = probe ? 1 : 0;
   p.tokens = dev_tokens; p.n_tokens = n; p.layers_used = layers_used; p.out_tokens = dev_argmax; p.out_margin = dev_margin;
-  int rc = launch(c, p, s);
+  rc = launch(c, p, s);
   if (rc != LS_OK) return rc;
   c->prefilled = false; c->drafted = false;
   LsState st;

@@ -407,6 +407,22 @@ def test_expired_wait_is_reported_and_the_next_prompt_recovers():
     gm.close()
 
 
+def test_scoring_recovers_from_an_expired_wait():
+    """The same for ls_score as the next call: it starts from rebuilt counters and a cleared error flag."""
+    from paper_2404_16710_amd.binding import LsError
+    w = CASES["c1"]
+    ws, prompt, om, gm = _setup(w)
+    want, margins = gm.score(prompt)
+    gm.debug_spin_limit(1)
+    with pytest.raises(LsError) as ei:
+        gm.generate(prompt, w.n_new, w.exit_layer, w.draft_len)
+    assert ei.value.code == -6
+    gm.debug_spin_limit(0)
+    got, m = gm.score(prompt)
+    assert list(got) == list(want) and list(m) == list(margins)
+    gm.close()
+
+
 @pytest.mark.parametrize("name", ["c1", "gqa-hd128-bf16", "gqa2-f32"])
 def test_generation_without_cache_reuse_matches(name):
     """ls_generate_no_reuse (ablation of Section 4.3.3): verification recomputes the early layers of the
