@@ -16,6 +16,7 @@
 
 extern "C" int ls_launch_program(const LsKParams* p, int dtype_is_bf16, int grid, hipStream_t stream);
 extern "C" int ls_kernel_setup(int dtype_is_bf16, int hd, int* max_blocks_per_cu);
+extern "C" int ls_launch_clear(void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_read(const void* src, size_t bytes, void* sink, int workgroups, hipStream_t stream);
 extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, int last_row, hipStream_t s);
@@ -137,7 +138,7 @@ void set_decomposition(ls_ctx* c) {
 }
 
 int launch(ls_ctx* c, LsKParams& p, hipStream_t s) {
-  if (hipMemsetAsync(p.bar, 0, 4096, s) != hipSuccess) return LS_E_HIP;
+  if (ls_launch_clear(p.bar, 4096, s) != 0) return LS_E_HIP;
   if (ls_launch_program(&p, c->cfg.dtype == LS_BF16, c->grid, s) != 0) return LS_E_HIP;
   return LS_OK;
 }
@@ -163,7 +164,7 @@ int read_state(ls_ctx* c, LsState* st, hipStream_t s) {
 // buffers, counters and state are contiguous in the workspace).
 int recover(ls_ctx* c, hipStream_t s) {
   if (!c->poisoned) return LS_OK;
-  if (hipMemsetAsync(c->ws + c->lay.xbuf, 0, c->lay.x_pf - c->lay.xbuf, s) != hipSuccess) return LS_E_HIP;
+  if (ls_launch_clear(c->ws + c->lay.xbuf, c->lay.x_pf - c->lay.xbuf, s) != 0) return LS_E_HIP;
   c->poisoned = false;
   c->prefilled = c->drafted = false;
   return LS_OK;

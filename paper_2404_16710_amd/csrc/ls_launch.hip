@@ -19,6 +19,20 @@ __global__ __launch_bounds__(256) void ls_copy_kernel(const uint4* __restrict__ 
     dst[i] = src[i];
 }
 
+// Clears counters and flags.  A kernel and not hipMemsetAsync, because a caller may capture ls_prefill, ls_draft and
+// ls_verify into a graph, and memset nodes of a graph have given wrong values on replays after the first on this platform.  (The same time: one launch
+// of one workgroup for the barrier's 4 KB.)
+__global__ __launch_bounds__(256) void ls_clear_kernel(uint4* dst, size_t n16) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
+    dst[i] = make_uint4(0, 0, 0, 0);
+}
+
+extern "C" int ls_launch_clear(void* dst, size_t bytes, hipStream_t stream) {   // (16-byte aligned, a multiple of 16)
+  const size_t n16 = bytes / 16, blocks = (n16 + 255) / 256;
+  ls_clear_kernel<<<dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, stream>>>(static_cast<uint4*>(dst), n16);
+  return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
 extern "C" int ls_launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream) {
   ls_copy_kernel<<<dim3(2048), dim3(256), 0, stream>>>(static_cast<const uint4*>(src), static_cast<uint4*>(dst), bytes / 16);
   return hipGetLastError() == hipSuccess ? 0 : 1;
