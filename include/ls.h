@@ -220,14 +220,25 @@ int ls_set_launch(ls_ctx *ctx, int32_t workgroups_per_cu);
 
 /* Shape of the prompt pass used by later calls.  Prompts of 32 or more ids run as GEMMs over all
  * rows of a chunk; kernel, output tile and the number of workgroups that share a tile's sum are chosen
- * by shape (rows = 0, the default); 32, 64 or 128 force the register-staged kernel (the default for
- * 32-bit models and widths that are not multiples of 64) with that tile height, 160 forces its 64-row
- * tiles that are 160 instead of 128 columns wide in the products into the residual rows (where 160
+ * by shape and by the room that the workspace has for partial sums (rows = 0, the default): a short prompt in
+ * a context of large max_seq spreads its sums over more workgroups than in one that it just fits, which is faster
+ * and orders the sums differently; 32, 64 or 128 force the register-staged kernel (the default for
+ * 32-bit models and for products over a width that is below 256 or not a multiple of 64) with that
+ * tile height, 160 forces its 64-row tiles that are 160 instead of 128 columns wide in the products into the residual rows (where 160
  * divides d_model; it picks them by itself when they fill the chip in fewer rounds), 16 sends every
  * prompt through the 16-row passes of the decode kernel.  All choices compute the same operation
  * and differ in the order of the floating-point sums only.  Host state only: no GPU work.
  * Returns LS_OK, LS_E_ARG for a null context or LS_E_RANGE for any other value. */
 int ls_set_prompt_tiles(ls_ctx *ctx, int32_t rows);
+
+/* Debug aid: the form of the default prompt pass's products in later calls.  tile 1 .. 6: output tiles of 256 x 256,
+ * 256 x 128, 128 x 128, 128 x 64, 64 x 128 or 64 x 64 rows x columns (gate and up columns counted apart); splits 1 .. 8:
+ * workgroups that share the sum of one tile of the products into the residual rows; 0: chosen by shape (the default of
+ * both).  Where a shape does not allow a form, the nearest that it does is taken: 64 x 64 tiles for Q, K and V when
+ * the tile's columns do not divide the two widths, fewer splits when K or the workspace holds no more.  Every form
+ * computes the same operation; the setting is for tests that run each of them.  Host state only: no GPU work.
+ * Returns LS_OK, LS_E_ARG for a null context or LS_E_RANGE. */
+int ls_debug_prompt_plan(ls_ctx *ctx, int32_t tile, int32_t splits);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture set-up, tight serving
  * loops, harnesses that forbid hipMalloc): ls_generate without a caller workspace and without a

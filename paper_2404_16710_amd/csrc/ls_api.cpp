@@ -301,6 +301,14 @@ int ls_set_prompt_tiles(ls_ctx* c, int32_t rows) {
   return LS_OK;
 }
 
+int ls_debug_prompt_plan(ls_ctx* c, int32_t tile, int32_t splits) {
+  if (!c) return LS_E_ARG;
+  if (tile < 0 || tile > 6 || splits < 0 || splits > 8) return LS_E_RANGE;
+  c->pf.mm_tile = tile;
+  c->pf.mm_splits = splits;
+  return LS_OK;
+}
+
 int ls_debug_spin_limit(ls_ctx* c, int32_t polls) {
   if (!c) return LS_E_ARG;
   if (polls < 0) return LS_E_RANGE;

@@ -20,8 +20,8 @@ __global__ __launch_bounds__(256) void ls_copy_kernel(const uint4* __restrict__ 
 }
 
 // Clears counters and flags.  A kernel and not hipMemsetAsync, because a caller may capture ls_prefill, ls_draft and
-// ls_verify into a graph, and memset nodes of a graph have given wrong values on replays after the first on this platform.  (The same time: one launch
-// of one workgroup for the barrier's 4 KB.)
+// ls_verify into a graph, and memset nodes of a graph have given wrong values on replays after the first on this
+// platform.  (The same time: one launch of one workgroup for the barrier's 4 KB.)
 __global__ __launch_bounds__(256) void ls_clear_kernel(uint4* dst, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
     dst[i] = make_uint4(0, 0, 0, 0);

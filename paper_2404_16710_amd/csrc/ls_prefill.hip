@@ -795,7 +795,7 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts
       if constexpr (sizeof(T) == 2) {
         PfMm g{};
         g.A = A; g.lda = K; g.W[0] = W; g.M = M; g.N = dm; g.K = K; g.x = p.x_pf; g.pos0 = pos0; g.hd = p.hd;
-        g.splits = 1;
+        g.splits = 1; g.force_tile = p.mm_tile; g.force_splits = p.mm_splits;
         const size_t piece = (size_t)M * dm * sizeof(float);
         add_parts(g, from, end, piece);
         add_parts(g, from2, end2, piece);
@@ -829,7 +829,7 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts
     if (mm) {
       const size_t lofs = (size_t)l * p.nkv * p.max_seq * p.hd;
       f.A = p.a_pf; f.lda = dm; f.M = M; f.K = dm; f.splits = 1; f.hd = p.hd; f.pos0 = pos0; f.max_seq = p.max_seq;
-      f.rope_cos = p.rope_cos; f.rope_sin = p.rope_sin;
+      f.rope_cos = p.rope_cos; f.rope_sin = p.rope_sin; f.force_tile = p.mm_tile;
       f.W[0] = W.wq; f.W[1] = W.wk; f.W[2] = W.wv; f.N = qd + 2 * kvd; f.N_q = qd; f.N_kv = kvd;
       f.out = p.q_pf; f.ldo = qd; f.out_k = static_cast<T*>(p.kcache) + lofs; f.out_v = static_cast<T*>(p.vcache) + lofs;
       if constexpr (sizeof(T) == 2) {
