@@ -9,11 +9,14 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-# rows, query heads, key/value heads, head_dim.  One wave of queries: few blocks (and a second chunk of 60 rows deep in
-# the cache); two: 500 rows x 32 heads, 449 x 40; four: 1999 x 32 and 2041 x 28 (heads not a multiple of 8).
+# rows, query heads, key/value heads, head_dim; which split a chunk takes on 256 compute units.  One wave of queries: few
+# blocks (and a second chunk of 60 rows deep in the cache); two: 500 rows x 32 heads, 449 x 40; four: 1999 x 32 and
+# 2041 x 28 (heads not a multiple of 8).  Second chunks after 2048 positions: 552 rows x 32 heads two, 652 x 28 two,
+# 1953 x 32 four, each head width.
 @pytest.mark.parametrize("n, nq, nkv, hd", [
     (32, 4, 4, 128), (33, 4, 1, 128), (127, 3, 3, 128), (129, 8, 2, 64), (2108, 2, 1, 64), (2108, 2, 2, 128),
-    (500, 32, 8, 64), (449, 40, 40, 128), (1025, 32, 8, 64), (1999, 32, 8, 128), (2041, 28, 28, 64)])
+    (500, 32, 8, 64), (449, 40, 40, 128), (1025, 32, 8, 64), (1999, 32, 8, 128), (2041, 28, 28, 64),
+    (2600, 32, 32, 64), (2600, 32, 8, 128), (2700, 28, 7, 128), (4001, 32, 8, 64), (4001, 32, 8, 128)])
 def test_prompt_attention_matches_the_row_passes(n, nq, nkv, hd):
     import torch
     from paper_2404_16710_amd import LsModel
