@@ -176,8 +176,8 @@ def test_rounds_replayed_from_oracle_state(name, E, d):
 @pytest.mark.parametrize("max_seq", [4096 + 512, 20000])
 def test_large_cache_capacity_groups_attention_tiles(name, max_seq):
     """With a large KV capacity one attention work item walks several 64-position tiles with a
-    running softmax (16-bit models: in the MFMA accumulators of each wave; the grouped-query case
-    has 24 query rows per KV head in its verify pass, i.e. two blocks of 16); the result must not
+    running softmax (16-bit models: in the MFMA accumulators of each wave; the 24 query rows per KV head
+    of the grouped-query case's verify pass are dealt out in blocks of 4); the result must not
     change."""
     w = CASES[name].with_(n_prompt=150, n_new=40)
     ws, prompt, om, gm = _setup(w, max_seq=max_seq)
