@@ -546,6 +546,8 @@ __global__ __launch_bounds__(256, 2) void pf_gemm_ks_kernel(const PfGemm g) {
   }
 }
 
+// The register-staged kernels above serve fp32 models, the products of 16-bit models over a width that is not a multiple
+// of 64 or below 256 (mm_fits), and the shapes that ls_set_prompt_tiles forces.
 // Few 128 x 128 tiles (a short prompt) leave most compute units without work: then 32-row tiles.
 // Both kernels are bound by how fast a compute unit takes in its operand tiles (one K step in
 // flight per workgroup), so the small tile's lower reuse only pays below about half a tile per
@@ -773,7 +775,8 @@ hipError_t launch_attn(const LsPfParams& p, int layer, int pos0, int M, hipStrea
 }
 
 // Room for partial sums [M][dm] of a split product in buffers of the prompt pass that are idle during it: whole
-// pieces of `from` .. `end` (contiguous in the workspace).
+// pieces of `from` .. `end` (contiguous in the workspace).  The buffers have min(max_seq, 2048) rows, so a prompt shorter
+// than that has room for more splits in a larger context.
 static void add_parts(PfMm& g, const void* from, const void* end, size_t piece) {
   const char* p = static_cast<const char*>(from);
   for (; g.splits - 1 < kMmParts && p + piece <= static_cast<const char*>(end); p += piece, ++g.splits)
