@@ -20,6 +20,8 @@ extern "C" int ls_launch_clear(void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
 extern "C" int ls_launch_read(const void* src, size_t bytes, void* sink, int workgroups, hipStream_t stream);
 extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layers, int pos0, int M, int last_row, hipStream_t s);
+extern "C" int ls_score_fits(const LsPfParams* p, int rows);
+extern "C" int ls_score_rows(const LsPfParams* p, const LsLayerW* host_layers, const LsScore* sc, int chunk, hipStream_t s);
 extern "C" int ls_static_scratch_ptr(void** ptr);
 
 namespace {
@@ -33,6 +35,7 @@ struct Layout {
 constexpr int kMaxGrid = 1024;
 constexpr int kPrefillRows = 2048;   // prompt rows the GEMM prefill handles per chunk
 constexpr int kPrefillMinRows = 32;  // shorter prompts take the 16-row passes of the decode kernel
+constexpr int kScoreMinRows = 17;    // texts that take more than one 16-row pass are scored in wide passes where the model allows it
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -479,11 +482,21 @@ static int score_impl(ls_ctx* c, const int32_t* dev_tokens, int32_t n, int32_t l
   hipStream_t s = static_cast<hipStream_t>(stream);
   int rc = recover(c, s);
   if (rc != LS_OK) return rc;
-  LsKParams p = program(c, LS_PROG_SCORE);
-  p.probe = probe ? 1 : 0;
-  p.tokens = dev_tokens; p.n_tokens = n; p.layers_used = layers_used; p.out_tokens = dev_argmax; p.out_margin = dev_margin;
-  rc = launch(c, p, s);
-  if (rc != LS_OK) return rc;
+  if (c->gemm_prefill && c->prof == nullptr && n >= kScoreMinRows && ls_score_fits(&c->pf, n < c->lay.pf_rows ? n : c->lay.pf_rows)) {
+    LsPfParams f = c->pf;
+    f.ssq_nt = c->base.ssq_nt; f.tokens = dev_tokens; f.layers_used = layers_used; f.capture = c->capture;
+    LsScore sc{};
+    sc.n_tokens = n; sc.probe = probe ? 1 : 0; sc.attn_ctiles = c->base.attn_ctiles; sc.x_tiles = c->base.x_tiles;
+    sc.attn_scale = c->base.attn_scale; sc.final_norm = c->base.final_norm; sc.lm_head = c->base.lm_head;
+    sc.out_tokens = dev_argmax; sc.out_margin = dev_margin; sc.state = c->base.state;
+    if (ls_score_rows(&f, c->host_layers.data(), &sc, c->lay.pf_rows, s) != 0) return LS_E_HIP;
+  } else {
+    LsKParams p = program(c, LS_PROG_SCORE);
+    p.probe = probe ? 1 : 0;
+    p.tokens = dev_tokens; p.n_tokens = n; p.layers_used = layers_used; p.out_tokens = dev_argmax; p.out_margin = dev_margin;
+    rc = launch(c, p, s);
+    if (rc != LS_OK) return rc;
+  }
   c->prefilled = false; c->drafted = false;
   LsState st;
   rc = read_state(c, &st, s);

@@ -115,4 +115,15 @@ struct LsPfParams {
   int32_t mm_tile, mm_splits;  // ls_debug_prompt_plan: tile (1..6) and K splits asked for; 0 = chosen by shape
 };
 
+// A scoring pass over all rows together (ls_score.inc).
+struct LsScore {
+  int32_t n_tokens, probe;
+  int32_t attn_ctiles, x_tiles;       // LsKParams: what the order of the decode kernels' sums depends on
+  float attn_scale;
+  const void *final_norm, *lm_head;
+  int32_t *out_tokens;
+  float *out_margin;
+  LsState *state;
+};
+
 #endif

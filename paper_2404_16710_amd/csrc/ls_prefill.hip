@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "ls_internal.h"
+#include "ls_lanes.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -191,7 +192,8 @@ __global__ __launch_bounds__(256) void pf_finish_kernel(const float* x, const Pf
 // of the tile width there, so a tile never straddles two matrices).  Three launches of 640 tiles each
 // (13B shape, 1024 prompt rows) fill the 512 resident workgroups one and a quarter times each; one
 // launch of 1920 tiles fills them three and three quarter times.
-enum { EPI_ROPE_Q = 0, EPI_ROPE_K = 1, EPI_V = 2, EPI_RESID = 3, EPI_GU = 4, EPI_QKV = 5 };
+// EPI_HEAD: the LM head of a scoring pass; its epilogue keeps every row's best column and runner-up.
+enum { EPI_ROPE_Q = 0, EPI_ROPE_K = 1, EPI_V = 2, EPI_RESID = 3, EPI_GU = 4, EPI_QKV = 5, EPI_HEAD = 6 };
 
 struct PfGemm {
   const void* A;    // [M][K] activations (model dtype), row stride lda
@@ -876,6 +878,8 @@ int run_layers(const LsPfParams& p, const LsLayerW* lw, int pos0, int M, PfParts
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
+#include "ls_score.inc"
+
 }  // namespace
 
 // Runs layers 0..layers_used-1 over rows [pos0, pos0+M) of the prompt (M <= pf_rows) and, after the last chunk,
@@ -886,5 +890,25 @@ extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layer
                             : run_layers<float>(*p, host_layers, pos0, M, parts, s);
   if (rc != 0 || last_row < 0) return rc;
   pf_finish_kernel<<<dim3((p->ssq_nt + 3) / 4), dim3(256), 0, s>>>(p->x_pf, parts, (size_t)last_row * p->dm, p->xbuf, p->ssq, p->dm, p->ssq_nt);
+  return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+// Whether a model's texts can be scored in wide passes: 16-bit, every product over a width that pf_mm_kernel takes, rows
+// that the norm keeps in LDS, and room for the candidates of `rows` rows (of the narrowest tile) where q, o and the SwiGLU
+// rows are.
+extern "C" int ls_score_fits(const LsPfParams* p, int rows) {
+  if (!p->is_bf16 || !mm_fits(p->dm, 2) || !mm_fits(p->qd, 2) || !mm_fits(p->ffn, 2) || p->dm > kScMaxWidth) return 0;
+  const size_t room = (size_t)(static_cast<const char*>(p->pf_end) - static_cast<const char*>(p->q_pf));
+  return (size_t)rows * ((p->vocab + 63) / 64) * sizeof(float4) <= room;
+}
+
+// The text's rows in chunks of `chunk` rows, then the state of a finished scoring pass.
+extern "C" int ls_score_rows(const LsPfParams* p, const LsLayerW* host_layers, const LsScore* sc, int chunk, hipStream_t s) {
+  for (int pos0 = 0; pos0 < sc->n_tokens; pos0 += chunk) {
+    const int M = sc->n_tokens - pos0 < chunk ? sc->n_tokens - pos0 : chunk;
+    const int rc = p->hd == 128 ? score_rows<128>(*p, host_layers, *sc, pos0, M, s) : score_rows<64>(*p, host_layers, *sc, pos0, M, s);
+    if (rc != 0) return rc;
+  }
+  sc_state_kernel<<<dim3(1), dim3(64), 0, s>>>(sc->state);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
