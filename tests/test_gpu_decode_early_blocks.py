@@ -1,6 +1,6 @@
 """Weights requested into LDS ahead of a stage's barrier: widths just over one round of blocks (a second round exists, its last
-block is partial), residual rows in one and in two tiles, and passes whose rows just leave the upper half of the input region
-free (8 rows of 2064 columns, 16 of 1040) and just do not (9 rows).  Self-speculative ids equal the one-row greedy ids, and
+block is partial), residual rows in one and in two tiles, and passes whose rows just fit ahead of the early blocks (4 rows of
+2064 columns, 8 of 1040, in 32 KB) and just do not (5 and 9 rows).  Self-speculative ids equal the one-row greedy ids, and
 both the oracle's up to near-ties."""
 import numpy as np
 import pytest
@@ -30,7 +30,7 @@ def test_early_blocks_keep_the_ids(name):
     gm = LsModel(m, ws, max_seq=w.n_prompt + w.n_new + 17)
     ar, _ = gm.generate(prompt, w.n_new, 0, 0)
     same_until_near_tie(ar[:8], ref.tokens, ref.margins)
-    for d in (1, 7, 8, 15):
+    for d in (1, 3, 4, 7, 8, 15):
         toks, _ = gm.generate(prompt, w.n_new, 1, d)
         assert toks == ar, d
     gm.close()
