@@ -124,6 +124,8 @@ struct LsScore {
   int32_t *out_tokens;
   float *out_margin;
   LsState *state;
+  int32_t prompt, eos, max_new;       // a prompt's rows: ends with the state of a finished prompt pass, first token to out_first
+  int32_t *out_first;                 // (may be null)
 };
 
 #endif

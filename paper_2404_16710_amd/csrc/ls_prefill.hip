@@ -909,6 +909,7 @@ extern "C" int ls_score_rows(const LsPfParams* p, const LsLayerW* host_layers, c
     const int rc = p->hd == 128 ? score_rows<128>(*p, host_layers, *sc, pos0, M, s) : score_rows<64>(*p, host_layers, *sc, pos0, M, s);
     if (rc != 0) return rc;
   }
-  sc_state_kernel<<<dim3(1), dim3(64), 0, s>>>(sc->state);
+  if (sc->prompt) sc_prompt_state_kernel<<<dim3(1), dim3(64), 0, s>>>(sc->state, sc->out_tokens, sc->out_margin, sc->n_tokens, sc->eos, sc->max_new, sc->out_first);
+  else sc_state_kernel<<<dim3(1), dim3(64), 0, s>>>(sc->state);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
