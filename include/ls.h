@@ -226,7 +226,9 @@ int ls_set_launch(ls_ctx *ctx, int32_t workgroups_per_cu);
  * 32-bit models and for products over a width that is below 256 or not a multiple of 64) with that
  * tile height, 160 forces its 64-row tiles that are 160 instead of 128 columns wide in the products into the residual rows (where 160
  * divides d_model; it picks them by itself when they fill the chip in fewer rounds), 16 sends every
- * prompt through the 16-row passes of the decode kernel.  All choices compute the same operation
+ * prompt, and every text of ls_score and ls_probe_layers, through the 16-row passes of the decode kernel; otherwise
+ * texts of more than 16 ids, and (rows = 0) prompts of 17 to 31, go through a layer together where a 16-bit model's widths
+ * are multiples of 64 of at least 256, with the sums of the 16-row passes bit for bit.  All choices compute the same operation
  * and differ in the order of the floating-point sums only.  Host state only: no GPU work.
  * Returns LS_OK, LS_E_ARG for a null context or LS_E_RANGE for any other value. */
 int ls_set_prompt_tiles(ls_ctx *ctx, int32_t rows);
