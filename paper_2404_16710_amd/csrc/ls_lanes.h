@@ -1,5 +1,5 @@
-// Exchanges between the lanes of a wave, and the candidates of an argmax.  Shared by the decode kernels and by the wide
-// scoring pass, which reproduces their sums bit for bit.
+// Exchanges between the lanes of a wave, sums of a few products, and the candidates of an argmax.  Shared by the decode
+// kernels and by the wide passes, which reproduce their sums bit for bit.
 #ifndef LS_LANES_H_
 #define LS_LANES_H_
 
@@ -46,6 +46,18 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += lane_xor1(v);
   v += lane_xor2(v);
   return wave_combine_quads(v, [](float a, float b) { return a + b; });
+}
+
+// Sums of products that the wide passes share with the decode kernels, with the fused steps written out: in a * x + b * y
+// either product may be the one that is rounded, and what a compiler picks may change with the code around it.
+__device__ __forceinline__ float sum2(float a, float x, float b, float y) { return __builtin_fmaf(a, x, b * y); }
+__device__ __forceinline__ float sum_of_squares(float x, float y, float z, float w) {
+  return __builtin_fmaf(w, w, __builtin_fmaf(z, z, sum2(x, x, y, y)));
+}
+// (a, b) turned by the angle with cosine c and sine s.
+__device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, float& lo, float& hi) {
+  lo = sum2(a, c, -b, s);
+  hi = sum2(a, s, b, c);
 }
 
 // Candidate of a row's argmax: highest value, its index (the lowest on ties), and the runner-up's value.
