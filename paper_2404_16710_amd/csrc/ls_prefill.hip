@@ -893,6 +893,14 @@ extern "C" int ls_prefill_layers(const LsPfParams* p, const LsLayerW* host_layer
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
+// Host only, for tests: the tile (0 .. 5, MmChoice) of a product's columns 0 .. first - 1, its splits, `first`, and the tile of
+// the columns behind them (-1: there are none).
+extern "C" void ls_mm_plan(int M, int n_out, int cols_per_out, int K, int cols_q, int cols_kv, int max_splits, int n_cu,
+                           int chains, int32_t* out) {
+  const MmChoice c = mm_choose(M, n_out, cols_per_out, K, cols_q, cols_kv, max_splits, n_cu, 0, 0, chains != 0);
+  out[0] = c.tile; out[1] = c.splits; out[2] = c.first; out[3] = c.rest;
+}
+
 // Whether a model's texts can be scored in wide passes: 16-bit, every product over a width that pf_mm_kernel takes, rows
 // that the norm keeps in LDS, and room for the candidates of `rows` rows (of the narrowest tile) where q, o and the SwiGLU
 // rows are.
