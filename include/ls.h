@@ -233,11 +233,13 @@ int ls_set_launch(ls_ctx *ctx, int32_t workgroups_per_cu);
  * Returns LS_OK, LS_E_ARG for a null context or LS_E_RANGE for any other value. */
 int ls_set_prompt_tiles(ls_ctx *ctx, int32_t rows);
 
-/* Debug aid: the form of the default prompt pass's products in later calls.  tile 1 .. 6: output tiles of 256 x 256,
+/* Debug aid: the form of the products of the default prompt pass, and of the passes that take a text's rows together, in
+ * later calls.  tile 1 .. 6: output tiles of 256 x 256,
  * 256 x 128, 128 x 128, 128 x 64, 64 x 128 or 64 x 64 rows x columns (gate and up columns counted apart); splits 1 .. 8:
  * workgroups that share the sum of one tile of the products into the residual rows; 0: chosen by shape (the default of
  * both).  Where a shape does not allow a form, the nearest that it does is taken: 64 x 64 tiles for Q, K and V when
- * the tile's columns do not divide the two widths, fewer splits when K or the workspace holds no more.  Every form
+ * the tile's columns do not divide the two widths, 64 x 64 instead of 256 x 256 and no splits where the sums are those of
+ * the 16-row passes, fewer splits when K or the workspace holds no more.  Every form
  * computes the same operation; the setting is for tests that run each of them.  Host state only: no GPU work.
  * Returns LS_OK, LS_E_ARG for a null context or LS_E_RANGE. */
 int ls_debug_prompt_plan(ls_ctx *ctx, int32_t tile, int32_t splits);

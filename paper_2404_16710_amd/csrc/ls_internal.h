@@ -112,7 +112,7 @@ struct LsPfParams {
   float *xbuf, *ssq;           // decode residual row 0 and its statistics (target of the finish step)
   float *capture;
   int32_t tile_rows;           // rows of a prompt GEMM's output tile: 0 = chosen by shape, else 32, 64, 128 or 160
-  int32_t mm_tile, mm_splits;  // ls_debug_prompt_plan: tile (1..6) and K splits asked for; 0 = chosen by shape
+  int32_t mm_tile, mm_splits;  // ls_debug_prompt_plan: tile (1..6) and K splits asked for; 0 = chosen by shape (wide passes: the tile only)
 };
 
 // A scoring pass over all rows together (ls_score.inc).

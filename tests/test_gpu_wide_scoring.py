@@ -1,7 +1,10 @@
 """Scoring and the layer probe in wide passes give the bits of the decode kernels' 16-row passes: predictions, margins
 and every layer's hidden states, over what decides the order of a sum there (items of one and of several attention
 tiles, one and two tiles of residual rows to a workgroup, both head widths, query groups, an odd number of K steps) and over
-what decides tiles here (ragged rows and columns, several chunks)."""
+what decides tiles here (ragged rows and columns, several chunks, every tile in every product, products that two tiles
+cover)."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -30,27 +33,67 @@ CASES = [(_case("rows17", 17), 64), (_case("rows33", 33), 34), (_case("rows257",
          (_case("chunks", 2100, n_layers=2, n_q_heads=2, n_kv_heads=1, d_model=256, ffn_dim=448), 2200)]
 
 
+def _passes(gm, text, rows, tile=0):
+    gm.set_prompt_tiles(rows)
+    gm.debug_prompt_plan(tile, 0)
+    cap = gm.debug_capture(True)
+    ids, margins = gm.score(text)
+    hidden = cap.cpu().numpy()[:, :len(text)].copy()
+    gm.debug_capture(False)
+    return hidden, ids, margins, gm.score(text, 1), gm.probe_layers(text), gm.get_state()
+
+
+def _assert_same(want, got, what=""):
+    for l, (a, b) in enumerate(zip(want[0], got[0])):
+        assert np.array_equal(a, b), (l, what)
+    assert np.isfinite(want[2]).all()
+    assert np.array_equal(want[1], got[1]) and np.array_equal(want[2], got[2]), what
+    for a, b in zip(want[3] + want[4], got[3] + got[4]):
+        assert np.array_equal(a, b), what
+    assert want[5] == got[5]
+
+
 @pytest.mark.parametrize("w,max_seq", CASES, ids=lambda x: x.model.name if hasattr(x, "model") else str(x))
 def test_wide_passes_have_the_bits_of_16_row_passes(w, max_seq):
     from paper_2404_16710_amd import LsModel
     ws, text = W.make_weights(w), W.make_prompt(w)
     gm = LsModel(w.model, ws, max_seq=max_seq)
-    n, L = len(text), w.model.n_layers
+    _assert_same(_passes(gm, text, 16), _passes(gm, text, 0))
+    gm.close()
 
-    def passes(rows):
-        gm.set_prompt_tiles(rows)
-        cap = gm.debug_capture(True)
-        ids, margins = gm.score(text)
-        hidden = cap.cpu().numpy()[:, :n].copy()
-        gm.debug_capture(False)
-        return hidden, ids, margins, gm.score(text, 1), gm.probe_layers(text), gm.get_state()
 
-    want, got = passes(16), passes(0)
-    for l in range(L):
-        assert np.array_equal(want[0][l], got[0][l]), l
-    assert np.isfinite(want[2]).all()
-    assert np.array_equal(want[1], got[1]) and np.array_equal(want[2], got[2])
-    for a, b in zip(want[3] + want[4], got[3] + got[4]):
-        assert np.array_equal(a, b)
-    assert want[5] == got[5]
+# Every tile that takes such sums, in the four products of a layer and in the head.  Pairs of steps along K in Q/K/V, gate/up and
+# head; O; down: 8, 8, 23; 7, 6, 18; 5, 4, 9, i.e. chains of none to three blocks, the last block whole and half; the
+# 128 columns that a tile is wide divide the q and the k/v widths, and a ragged tile is left in rows, d_model, ffn and vocabulary.
+@pytest.mark.parametrize("w", [_case("pairs8", 300), _case("pairs7", 300, n_layers=2, d_model=448, n_q_heads=3, n_kv_heads=3, ffn_dim=1152),
+                               _case("pairs5", 270, n_layers=2, d_model=320, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn_dim=576)],
+                         ids=lambda w: w.model.name)
+def test_every_tile_has_the_bits_of_16_row_passes(w):
+    from paper_2404_16710_amd import LsModel
+    ws, text = W.make_weights(w), W.make_prompt(w)
+    gm = LsModel(w.model, ws, max_seq=320)
+    want = _passes(gm, text, 16)
+    for tile in range(2, 7):
+        _assert_same(want, _passes(gm, text, 0, tile), tile)
+    gm.close()
+
+
+# gate/up in 256 x 128 tiles and 64 x 128 behind them; Q/K/V the same, with the change within K
+@pytest.mark.parametrize("w", [_case("gate_up", 1200, n_layers=1, d_model=1280, n_q_heads=2, n_kv_heads=1, ffn_dim=4928),
+                               _case("qkv", 658, n_layers=1, d_model=1280, n_q_heads=43, n_kv_heads=43, ffn_dim=320)],
+                         ids=lambda w: w.model.name)
+def test_two_tiles_have_the_bits_of_16_row_passes(w):
+    import torch
+    from paper_2404_16710_amd import LsModel, lib
+    m, plan = w.model, (ctypes.c_int32 * 4)()
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if m.name == "gate_up":
+        lib().ls_mm_plan(w.n_prompt, m.ffn_dim, 2, m.d_model, 0, 0, 1, n_cu, 1, plan)
+    else:
+        lib().ls_mm_plan(w.n_prompt, m.q_dim + 2 * m.kv_dim, 1, m.d_model, m.q_dim, m.kv_dim, 1, n_cu, 1, plan)
+        assert m.q_dim < plan[2] < m.q_dim + m.kv_dim
+    assert plan[3] >= 0
+    ws, text = W.make_weights(w), W.make_prompt(w)
+    gm = LsModel(m, ws, max_seq=w.n_prompt + 20)
+    _assert_same(_passes(gm, text, 16), _passes(gm, text, 0))
     gm.close()
