@@ -7,11 +7,12 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_prompt", [20, 70])               # 16-row passes, and the prompt pass
-def test_replays_of_a_captured_round_repeat_it(n_prompt):
+# 16-row passes, the prompt pass, and (widths that are multiples of 64) a short prompt's rows together and the prompt pass
+@pytest.mark.parametrize("n_prompt, ffn_dim", [(20, 1040), (70, 1040), (20, 1088), (70, 1088)])
+def test_replays_of_a_captured_round_repeat_it(n_prompt, ffn_dim):
     import torch
     from paper_2404_16710_amd import LsModel
-    m = W.ModelConfig(name="graph", n_layers=3, n_q_heads=4, n_kv_heads=2, head_dim=128, d_model=384, ffn_dim=1040,
+    m = W.ModelConfig(name="graph", n_layers=3, n_q_heads=4, n_kv_heads=2, head_dim=128, d_model=384, ffn_dim=ffn_dim,
                       vocab=1040, rope_base=10000.0, rms_eps=1e-5, dtype="bf16")
     w = W.Workload(m, exit_layer=1, draft_len=5, n_prompt=n_prompt, n_new=8, resid_scale=0.1, gain_jitter=0.1)
     ws, prompt = W.make_weights(w), W.make_prompt(w)

@@ -8,7 +8,7 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_prompt", [16, 17, 31, 32])
+@pytest.mark.parametrize("n_prompt", [17, 24, 31])
 @pytest.mark.parametrize("heads", [(4, 2, 128), (6, 2, 64)])
 def test_short_prompts_in_one_wide_pass(n_prompt, heads):
     from paper_2404_16710_amd import LsModel
@@ -36,7 +36,6 @@ def test_short_prompts_in_one_wide_pass(n_prompt, heads):
         return hidden, out
 
     want, got = passes(16), passes(0)
-    if n_prompt < 32:                                   # (longer prompts take sums in another order)
-        assert np.array_equal(want[0], got[0])
-        assert want[1] == got[1]
+    assert np.array_equal(want[0], got[0])
+    assert want[1] == got[1]
     gm.close()
