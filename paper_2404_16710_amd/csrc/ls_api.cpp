@@ -207,7 +207,7 @@ static int init_ctx(ls_ctx* c, const ls_config* cfg, const ls_weights* w, void* 
   c->capture = nullptr;
   c->prof = nullptr; c->prof_cap = 0; c->prof_wg = 0;
   c->prefilled = c->drafted = false;
-c->kv_policy = 0;
+  c->kv_policy = 0;
   c->poisoned = false;
   c->pos_bound = 0;
 

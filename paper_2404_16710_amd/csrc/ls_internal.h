@@ -7,7 +7,7 @@
 
 #define LS_THREADS 256          // workgroup size of the persistent kernel (4 wavefronts)
 #define LS_WAVES (LS_THREADS / 64)
-#define LS_SLOTS 4              // 256-byte weight blocks per wave kept in flight (per tile: LS_SLOTS / tiles)
+#define LS_SLOTS 4              // 256-byte weight blocks per wave kept in flight (per tile: LS_SLOTS / tiles; two tiles of residual rows: 3 each)
 #define LS_ROWS 16              // rows per pass (MFMA N dimension)
 #define LS_ATTN_TILE 64         // KV positions per attention work item
 #define LS_ACT_BYTES (128 * 1024) // LDS bytes for staged matmul inputs
