@@ -1,7 +1,7 @@
 """Products of the prompt pass that fill many rounds of workgroups: in one launch (gate/up with 130 columns of 256 x 256
 tiles, Q/K/V with 99 of 128 x 128), and covered by two tiles, whole rounds of the larger and the rest in a launch of the
-smaller.  The latter with every tile that the rest may have, ragged last tiles in rows and columns, and a Q/K/V product
-whose columns change tile within V.  Reference: the CPU oracle; and for two tiles the same product in 64 x 64 tiles
+smaller.  The latter with every pair of tiles that the rule is known to take, ragged last tiles in rows and columns, and Q/K/V
+products whose columns change tile within V and within K.  Reference: the CPU oracle; and for two tiles the same product in 64 x 64 tiles
 alone, whose sums are the same, bit for bit."""
 import ctypes
 
@@ -22,10 +22,12 @@ def _case(name, n_prompt, **kw):
 
 
 ONE = [_case("gate_up", 1999, ffn_dim=130 * 128 - 64), _case("qkv", 1999, n_q_heads=33, n_kv_heads=33)]
-# the workload, and the tile of the rest (1: 256 x 128, 2: 128 x 128, 4: 64 x 128, 5: 64 x 64)
-TWO = [(_case("gate_up_1", 1537, d_model=448, ffn_dim=11392), 1), (_case("gate_up_2", 1537, d_model=576, ffn_dim=7056), 2),
-       (_case("gate_up_4", 900, d_model=448, ffn_dim=10320), 4), (_case("gate_up_5", 1537, d_model=512, ffn_dim=5072), 5),
-       (_case("qkv_5", 1537, d_model=512, n_q_heads=48, n_kv_heads=16), 5)]
+# the workload, and its two tiles (0: 256 x 256, 1: 256 x 128, 2: 128 x 128, 3: 128 x 64, 5: 64 x 64)
+TWO = [(_case("gate_up_01", 1537, d_model=704, ffn_dim=10608), (0, 1)), (_case("gate_up_02", 1537, d_model=960, ffn_dim=7024), (0, 2)),
+       (_case("gate_up_03", 1537, d_model=576, ffn_dim=10320), (0, 3)), (_case("gate_up_05", 1537, d_model=960, ffn_dim=5040), (0, 5)),
+       (_case("gate_up_15", 1537, d_model=1280, ffn_dim=2512), (1, 5)), (_case("gate_up_25", 257, d_model=2048, ffn_dim=11472), (2, 5)),
+       (_case("qkv_05", 1537, d_model=960, n_q_heads=48, n_kv_heads=16), (0, 5)),
+       (_case("qkv_15", 777, d_model=1280, n_q_heads=52, n_kv_heads=13), (1, 5))]
 _id = lambda x: x.model.name if hasattr(x, "model") else ""
 
 
@@ -40,15 +42,17 @@ def _plan(w, n_cu):
     return list(out)
 
 
-@pytest.mark.parametrize("w,rest", TWO + [(w, -1) for w in ONE], ids=_id)
-def test_plans_take_the_tiles_they_are_named_after(w, rest):
-    tile, splits, first, r = _plan(w, 256)
+@pytest.mark.parametrize("w,tiles", TWO + [(w, None) for w in ONE], ids=_id)
+def test_plans_take_the_tiles_they_are_named_after(w, tiles):
+    tile, splits, first, rest = _plan(w, 256)
     m = w.model
     n_out = m.ffn_dim if m.name.startswith("gate_up") else m.q_dim + 2 * m.kv_dim
-    assert (r, splits) == (rest, 1)
-    assert (first == n_out) if rest < 0 else (0 < first < n_out and tile < rest)
-    if m.name == "qkv_5":
+    assert splits == 1
+    assert (rest < 0 and first == n_out) if tiles is None else ((tile, rest) == tiles and 0 < first < n_out)
+    if m.name == "qkv_05":
         assert m.q_dim + m.kv_dim < first
+    if m.name == "qkv_15":
+        assert m.q_dim < first < m.q_dim + m.kv_dim
 
 
 def _hidden(gm, w, plan):

@@ -78,21 +78,22 @@ def test_every_tile_has_the_bits_of_16_row_passes(w):
     gm.close()
 
 
-# gate/up in 256 x 128 tiles and 64 x 128 behind them; Q/K/V the same, with the change within K
-@pytest.mark.parametrize("w", [_case("gate_up", 1200, n_layers=1, d_model=1280, n_q_heads=2, n_kv_heads=1, ffn_dim=4928),
-                               _case("qkv", 658, n_layers=1, d_model=1280, n_q_heads=43, n_kv_heads=43, ffn_dim=320)],
+# gate/up in tiles of 256 x 128 and of 128 x 128 with 64 x 64 behind them; Q/K/V in 256 x 128 and 64 x 64, with the change within K
+@pytest.mark.parametrize("w", [_case("gate_up_15", 1537, n_layers=1, d_model=1280, n_q_heads=2, n_kv_heads=1, ffn_dim=2560),
+                               _case("gate_up_25", 257, n_layers=1, d_model=2048, n_q_heads=2, n_kv_heads=1, ffn_dim=11520),
+                               _case("qkv_15", 777, n_layers=1, d_model=1280, n_q_heads=52, n_kv_heads=13, ffn_dim=320)],
                          ids=lambda w: w.model.name)
 def test_two_tiles_have_the_bits_of_16_row_passes(w):
     import torch
     from paper_2404_16710_amd import LsModel, lib
     m, plan = w.model, (ctypes.c_int32 * 4)()
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    if m.name == "gate_up":
+    if m.name.startswith("gate_up"):
         lib().ls_mm_plan(w.n_prompt, m.ffn_dim, 2, m.d_model, 0, 0, 1, n_cu, 1, plan)
     else:
         lib().ls_mm_plan(w.n_prompt, m.q_dim + 2 * m.kv_dim, 1, m.d_model, m.q_dim, m.kv_dim, 1, n_cu, 1, plan)
         assert m.q_dim < plan[2] < m.q_dim + m.kv_dim
-    assert plan[3] >= 0
+    assert (plan[0], plan[3]) == tuple(map(int, m.name[-2:]))
     ws, text = W.make_weights(w), W.make_prompt(w)
     gm = LsModel(m, ws, max_seq=w.n_prompt + 20)
     _assert_same(_passes(gm, text, 16), _passes(gm, text, 0))
